@@ -700,18 +700,27 @@ struct LocRegs {
     uint32_t k[2][8];
     uint32_t v[8];
 };
+// kRagged: the tile may reach past the end of the sequence.  The range check of a buffer load covers the
+// per-lane offset only, so the row goes there: row >= T gives an offset >= T row_bytes, which is past the
+// buffer's last byte (seq_span <= T row_bytes), and reads as zero.  Tiles that are known to be full carry the
+// row in the scalar offset (no address arithmetic per lane).
+template <bool kRagged>
 __device__ __forceinline__ void loc_load(LocRegs& r, const SeqRsrc& R, int t, int v0, int tid, uint32_t rk,
                                          uint32_t rv) {
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         const int item = tid + it * kThreads;
-        const uint32_t vo = (8 * (item / (kDQK / 2))) * rk + 4 * (item % (kDQK / 2));
+        const uint32_t row = 8 * (item / (kDQK / 2)), col = 4 * (item % (kDQK / 2));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r.k[it][j] = bload32(R.k, vo, static_cast<uint32_t>(t + j) * rk);
+        for (int j = 0; j < 8; ++j)
+            r.k[it][j] = kRagged ? bload32(R.k, (row + t + j) * rk + col, 0)
+                                 : bload32(R.k, row * rk + col, static_cast<uint32_t>(t + j) * rk);
     }
-    const uint32_t vo = (8 * (tid / (kDVT / 2))) * rv + 4 * (tid % (kDVT / 2));
+    const uint32_t row = 8 * (tid / (kDVT / 2)), col = 4 * (tid % (kDVT / 2));
 #pragma unroll
-    for (int j = 0; j < 8; ++j) r.v[j] = bload32(R.v, vo, static_cast<uint32_t>(t + j) * rv + v0 * 2);
+    for (int j = 0; j < 8; ++j)
+        r.v[j] = kRagged ? bload32(R.v, (row + t + j) * rv + col, v0 * 2)
+                         : bload32(R.v, row * rv + col, static_cast<uint32_t>(t + j) * rv + v0 * 2);
 }
 __device__ __forceinline__ void loc_store(uint16_t* Kt, uint16_t* Vt, const LocRegs& r, int tid) {
     u32x4_t c0, c1;
@@ -766,6 +775,7 @@ local_state_kernel(LocalArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     constexpr bool kHiLo = (kMode == kFwdHiLo);
     constexpr int NW = (kMode == kRev) ? 3 : 2;
+    constexpr bool kRagged = (kMode == kRev);   // the forward modes cover full segments only
     LocSmem<NW>& S = *reinterpret_cast<LocSmem<NW>*>(smem_raw);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -794,7 +804,7 @@ local_state_kernel(LocalArgs A) {
     }
 
     LocRegs rg;
-    if (ntok > 0) loc_load(rg, P, tb, v0, tid, A.rk, A.rv);   // first tile, in flight during the gate pass
+    if (ntok > 0) loc_load<kRagged>(rg, P, tb, v0, tid, A.rk, A.rv);   // first tile, in flight during the gate pass
 
     float xsum = 0.0f, mloc = 0.0f;   // the slot's last entries
     if constexpr (kMode == kRev) {
@@ -897,13 +907,13 @@ local_state_kernel(LocalArgs A) {
     const int nt = ntok / kLocTile;
     if (nt > 0) {
         loc_store(S.Kt[0], S.Vt[0], rg, tid);
-        if (nt > 1) loc_load(rg, P, tb + kLocTile, v0, tid, A.rk, A.rv);
+        if (nt > 1) loc_load<kRagged>(rg, P, tb + kLocTile, v0, tid, A.rk, A.rv);
     }
     for (int i = 0; i < nt; ++i) {
         __syncthreads();   // tile i and the weights are visible; the other buffer's readers are done
         if (i + 1 < nt) {
             loc_store(S.Kt[(i + 1) & 1], S.Vt[(i + 1) & 1], rg, tid);
-            if (i + 2 < nt) loc_load(rg, P, tb + (i + 2) * kLocTile, v0, tid, A.rk, A.rv);
+            if (i + 2 < nt) loc_load<kRagged>(rg, P, tb + (i + 2) * kLocTile, v0, tid, A.rk, A.rv);
         }
         const uint16_t* Kt = S.Kt[i & 1];
         const uint16_t* Vt = S.Vt[i & 1];
