@@ -4,6 +4,8 @@
 // the sequence addressing.  Everything lives in an anonymous namespace, so each translation unit that
 // includes this header has its own copy.
 #pragma once
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace mlstm {
@@ -36,8 +38,9 @@ struct Cfg {
     static constexpr int TP = L + 8;
 };
 
-// Per-chunk gate quantities, written one chunk ahead by the gate wave.
-template <int L>
+// Per-chunk gate quantities, written one chunk ahead by the gate wave.  kF32N: the n-update weights in fp32, for
+// the backward, which branches on |q . n + ...| against the floor, so that n's rounding decides rows close to it.
+template <int L, bool kF32N = false>
 struct alignas(16) GateBuf {
     float x2[L];        // (i~ - b) * log2 e
     float M2[L];        // M * log2 e (0 for a row with no input at all)
@@ -46,7 +49,7 @@ struct alignas(16) GateBuf {
     float interN[L];    // exp(m_prev - M) / sqrt(DQK):     scale of Q n
     float floorv[L];    // exp(-(b + M))
     float wC[L];        // C-update weights exp(x - M_L - s_new)
-    uint16_t wb[2][L];  // n-update weights exp(x - M_L) as bf16 hi / lo rows
+    std::conditional_t<kF32N, float[L], uint16_t[2][L]> wb;   // n-update weights exp(x - M_L): fp32, or bf16 hi / lo rows
     float scal[4];      // [0] n decay, [1] m_next, [2] s_new, [3] eager C scale (1: none)
 };
 
@@ -133,8 +136,8 @@ __device__ __forceinline__ void load_gates(float& gi, float& gf, const SeqRsrc& 
 // survive), every row keeps R, its last restart at or before it, and the row's maxima, weights
 // and entry-state terms cover only the tokens from R on.  A chunk that holds a restart drops
 // its entry state: C and n are scaled by zero before this chunk's keys are added.
-template <int L>
-__device__ __forceinline__ void gate_phase(GateBuf<L>& Gb, float gi, float gf, float& m_prev,
+template <int L, bool kF32N>
+__device__ __forceinline__ void gate_phase(GateBuf<L, kF32N>& Gb, float gi, float gf, float& m_prev,
                                            float& s_cur, int lane, int nvalid) {
     static_assert(L == 64, "one token per lane");
     const bool ok = lane < nvalid;
@@ -174,9 +177,13 @@ __device__ __forceinline__ void gate_phase(GateBuf<L>& Gb, float gi, float gf, f
         const bool none = (xx == -INFINITY) || (static_cast<float>(tau) < rL);
         Gb.wC[tau] = none ? 0.0f : fexp(xx - ML - s_new);
         const float wn = none ? 0.0f : fexp(xx - ML);
-        const uint16_t whi = f32_to_bf16(wn);
-        Gb.wb[0][tau] = whi;
-        Gb.wb[1][tau] = f32_to_bf16(wn - bf16_to_f32(whi));
+        if constexpr (kF32N) {
+            Gb.wb[tau] = wn;
+        } else {
+            const uint16_t whi = f32_to_bf16(wn);
+            Gb.wb[0][tau] = whi;
+            Gb.wb[1][tau] = f32_to_bf16(wn - bf16_to_f32(whi));
+        }
     };
     emit(lane, b, x, p, r);
     const float m_next = bL + ML;

@@ -343,6 +343,24 @@ __device__ __forceinline__ void dtile_update(DState& C, const uint16_t* Mt, cons
         }
     }
 }
+// The order of one dtile_update (half a chunk's) with its kTr transpose reads and kProducts products per pp: the
+// next chunk's load of a pp before its products, the operands one pp ahead.  Left to itself the compiler puts the
+// loads last, and the next chunk waits for them (x walk of 16 x 4096 tokens 854 us, 824 in this order).
+template <int kTr, int kProducts>
+__device__ __forceinline__ void dtile_update_order() {
+    __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, kTr + 4, 0);
+    __builtin_amdgcn_sched_group_barrier(0x8, kProducts, 0);
+    __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x8, kProducts, 0);
+    __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x8, kProducts, 0);
+    __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x8, kProducts, 0);
+    __builtin_amdgcn_sched_barrier(0);
+}
 // the tile from a segment slot (four rows interleaved: element (d, v) at slot_c4(d / 4, v) + d % 4)
 __device__ __forceinline__ void dtile_from_slot(DState& C, const float* slot, int d0, int vq, int lane) {
     const int l16 = lane & 15, g16 = lane >> 4;
@@ -374,16 +392,40 @@ __device__ __forceinline__ int64_t dtile_c0(int d0, int dt, int vq, int pp, int 
 // One workgroup of 8 waves per (sequence, 64-row d tile, segment), with the gate phase and lazy scale of
 // chunk_mfma_kernel<64> (C = C_acc e^{s}).  Per chunk: X^T = C dH^T with C as a bf16 pair hi + lo, then
 // C += (w e^{-s} K)^T V with the weighted keys as a bf16 pair (products to about 2^-17 rather than the 2^-9
-// of one rounding, because the backward's gradients can cancel against the state) and n the same.  The
+// of one rounding, because the backward's gradients can cancel against the state).  The
 // weights go on K, whose tile is 64 columns wide, rather than on V: half the operand reads of the update.
+// n is summed in fp32 from the fp32 weights and the keys themselves: q . n decides the branch |D| > floor, and
+// with n from the rounded pair (weights times e^{-s}, whose exponent is up to 20 larger) three times as many rows
+// of 1 x 2048-token calls fell on the wrong side of it.
 struct XSmem {
     uint16_t Vt[kDV * kTP];        // the chunk's V^T, rows in pair order
     uint16_t dH[kBL * kRP];        // the chunk's dH rows, then the exchange of the partial products
     uint16_t Kw[2][kBL * 68];      // w e^{-s} K rows of this d tile as bf16 hi, lo (136-byte pitch)
-    GateBuf<64> G[2];              // by chunk parity
-    float n[kDTile];               // fp32 normaliser of this d tile
+    GateBuf<64, true> G[2];        // by chunk parity
 };
 static_assert(sizeof(XSmem) <= 160 * 1024, "LDS budget");
+// the waves' partial sums of n (kWaves x 64 floats) take the place of the dH rows behind the exchange
+static_assert(kExBytes + kWaves * kDTile * 4 <= 64 * kRP * 2, "n partials");
+
+// x[0..7] of a lane are its columns 8 (lane % 8) + 0..7 of row lane / 8; the sum over the eight rows of column
+// 8 (lane % 8) + rows8_col(lane), one column per lane (each step halves the columns a lane still sums)
+__device__ __forceinline__ int rows8_col(int lane) { return 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1); }
+__device__ __forceinline__ float rows8_sum(const float (&x)[8], int lane) {
+    float y[4], z[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // lanes 0..31 keep columns 0..3, lanes 32..63 columns 4..7
+        const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + 4]), false, false);
+        y[i] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {   // even rows of 16 lanes keep the first two of their columns, odd ones the others
+        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(y[i]), __float_as_uint(y[i + 2]), false, false);
+        z[i] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    }
+    const bool odd = (lane & 8) != 0;
+    const float keep = odd ? z[1] : z[0], give = odd ? z[0] : z[1];
+    return keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), 0x128, 0xf, 0xf, false));   // row_ror:8
+}
 
 __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -438,7 +480,8 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
         nin = slot + kCV;
         m_prev = slot[kCV + kDQK + 2];
     }
-    if (tid < kDTile) S.n[tid] = nin ? nin[kDTile * tile + tid] : 0.0f;
+    // element `lane` of this d tile's normaliser, the same in every wave
+    float n = nin ? nin[kDTile * tile + lane] : 0.0f;
     float s_off = 0.0f;   // C = C_acc e^{s_off}
     float g_m = m_prev, g_s = 0.0f;
     float gi = 0.f, gf = 0.f;
@@ -458,27 +501,32 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
         load(t0, tid);
         load_rows512(rdhv, rdh, t0, tid);
         load_pieces<8>(rv, P.v, kDV * 2, t0, wave, lane);
-        if (gate_wave) gate_phase<64>(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
+        if (gate_wave) gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
         load_gates<64>(gi, gf, P, t0 + kBL, lane);   // gates are loaded a chunk before their phase
     }
     const int tid_outer = tid;
     for (int c = c_begin; c < c_end; ++c) {
         MLSTM_OPAQUE_LANES(tid_outer);
         const int t0 = c * kBL;
-        const GateBuf<64>& Gc = S.G[c & 1];
-        __syncthreads();   // the previous chunk's readers are done; this chunk's gates and n are visible
+        const GateBuf<64, true>& Gc = S.G[c & 1];
+        __syncthreads();   // the previous chunk's readers are done; this chunk's gates are visible
         store_rows512(S.dH, rdhv, tid);
         store_transposed<8>(S.Vt, rv, wave, lane);
+        float npart;   // this wave's eight rows of sum_t w_t k_t, columns 8 (lane % 8) + rows8_col of the tile
         {
             const int krow = tid >> 3, kcol = 8 * (tid & 7);
-            const float w = Gc.wC[krow];
+            const float w = Gc.wC[krow], wn = Gc.wb[krow];
             u32x4_t hi, lo;
+            float kn[8];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float a = lo_f32(rk[i]) * w, b = hi_f32(rk[i]) * w;
                 hi[i] = pack_bf16x2(a, b);
                 lo[i] = pack_bf16x2(a - lo_f32(hi[i]), b - hi_f32(hi[i]));
+                kn[2 * i] = lo_f32(rk[i]) * wn;
+                kn[2 * i + 1] = hi_f32(rk[i]) * wn;
             }
+            npart = rows8_sum(kn, lane);
             uint16_t* p0 = &S.Kw[0][krow * KP + kcol];   // 8-byte aligned rows
             uint16_t* p1 = &S.Kw[1][krow * KP + kcol];
             *reinterpret_cast<u32x2_t*>(p0) = u32x2_t{hi[0], hi[1]};
@@ -491,11 +539,11 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
         load(tn, tid);
         // n and m entering the chunk
         MLSTM_CHECK(c < A.NC, kDbgChunkBwd);
-        bstoref(rn, tid < kDTile ? static_cast<uint32_t>(c * kDQK + kDTile * tile + tid) * 4u : kNoStore, S.n[tid & (kDTile - 1)]);
+        bstoref(rn, tid < kDTile ? static_cast<uint32_t>(c * kDQK + kDTile * tile + tid) * 4u : kNoStore, n);
         bstoref(rm, tile == 0 && tid == 0 ? static_cast<uint32_t>(c) * 4u : kNoStore, m_prev);
         __syncthreads();   // the chunk's operands are visible
         // gates of the next chunk, one chunk ahead
-        if (gate_wave && c + 1 < c_end) gate_phase<64>(S.G[(c + 1) & 1], gi, gf, g_m, g_s, lane, A.T - (t0 + kBL));
+        if (gate_wave && c + 1 < c_end) gate_phase(S.G[(c + 1) & 1], gi, gf, g_m, g_s, lane, A.T - (t0 + kBL));
         load_gates<64>(gi, gf, P, t0 + 2 * kBL, lane);
 
         f32x4_t X[2][4];
@@ -517,9 +565,8 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
 #pragma unroll
                     for (int e = 0; e < 2; ++e) C[dt][pp][e] *= c_scale;
         }
-        const uint32_t one = l16 == 0 ? 0x3F803F80u : 0u;   // a row of ones: sums the weighted keys over tau
-        const u32x4_t ones = {one, one, one, one};
-        f32x4_t nacc[2] = {f32x4_t{}, f32x4_t{}};
+        float* np = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(S.dH) + kExBytes);
+        np[wave * kDTile + 8 * (lane & 7) + rows8_col(lane)] = npart;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             u32x4_t b[2][2];   // hi, lo
@@ -529,20 +576,13 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
                 for (int dt = 0; dt < 2; ++dt) b[p][dt] = tr_op(S.Kw[p], KP, 32 * ks, 32 * dp + 16 * dt, lane);
             dtile_update<2>(C, S.Vt, b, vq, ks, lane,
                             [&](int i) { rv[i] = load_piece<8>(P.v, kDV * 2, tn, i, wave, lane); });
-            if (vq == 0) {
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt) nacc[dt] = mfma16(ones, b[1][dt], mfma16(ones, b[0][dt], nacc[dt]));
-            }
+            dtile_update_order<8, 8>();
         }
-        if (vq == 0 && g16 == 0) {
-            const float en = expf(s_new);   // the weights carry e^{-s}
+        __syncthreads();   // the exchange and the partial sums of n are visible
+        float nsum = 0.0f;
 #pragma unroll
-            for (int dt = 0; dt < 2; ++dt) {
-                const int d = 32 * dp + 16 * dt + l16;
-                S.n[d] = decay_n * S.n[d] + nacc[dt][0] * en;
-            }
-        }
-        __syncthreads();   // the exchange is visible
+        for (int w = 0; w < kWaves; ++w) nsum += np[w * kDTile + lane];
+        n = decay_n * n + nsum;
         f32x4_t Y[2];
         dtile_take(Y, ex, X, vq, dp, lane);
         const int tau = 16 * vq + l16;

@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         load_qk<L>(rqk, P, t0, 0, tid, A.rq, A.rk);
         if (gate_wave) {
             load_gates<L>(gi, gf, P, t0, lane);
-            gate_phase<L>(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
+            gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
         }
         store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
         load_v_tr<L>(rv, P, t0, v0, wave, lane, A.rv);
@@ -525,7 +525,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         // barrier, so the gate wave issues ahead of its SIMD partner meanwhile
         if (gate_wave && c + 1 < c_end) {
             __builtin_amdgcn_s_setprio(1);
-            gate_phase<L>(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + L));
+            gate_phase(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + L));
             __builtin_amdgcn_s_setprio(0);
         }
 
@@ -759,6 +759,10 @@ struct LocalArgs {
     int NC;
 };
 enum LocalMode { kFwd, kFwdHiLo, kRev };
+// bf16 parts of the n weights: two (17 bits) for the prefill; three, all 24 bits, for the backward, whose branch
+// |D| > floor reads n
+template <LocalMode kMode>
+constexpr int kLocalParts = kMode == kFwd ? 2 : 3;
 
 // One workgroup per (sequence, local segment, sub-segment, dv tile); its slot receives C[:, tile],
 // and (dv tile 0) n, m_loc and the segment's logsig sum.  kFwdHiLo: the weighted values w v enter the
@@ -774,7 +778,7 @@ __global__ void __launch_bounds__(kThreads, 1) __attribute__((amdgpu_waves_per_e
 local_state_kernel(LocalArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     constexpr bool kHiLo = (kMode == kFwdHiLo);
-    constexpr int NW = (kMode == kRev) ? 3 : 2;
+    constexpr int NW = kLocalParts<kMode>;
     constexpr bool kRagged = (kMode == kRev);   // the forward modes cover full segments only
     LocSmem<NW>& S = *reinterpret_cast<LocSmem<NW>*>(smem_raw);
     const int tid = threadIdx.x;
@@ -889,8 +893,11 @@ local_state_kernel(LocalArgs A) {
             const float wv = (t < Rl || X == -INFINITY) ? 0.0f : fexp(S.w[t] - X);
             S.w[t] = wv;
             const uint16_t hi = f32_to_bf16(wv);
+            const float rest = wv - bf16_to_f32(hi);
+            const uint16_t lo = f32_to_bf16(rest);
             S.wb[0][t] = hi;
-            S.wb[1][t] = f32_to_bf16(wv - bf16_to_f32(hi));
+            S.wb[1][t] = lo;
+            if constexpr (NW == 3) S.wb[2][t] = f32_to_bf16(rest - bf16_to_f32(lo));
         }
         mloc = carry + X;   // -inf for an empty sub-segment
         xsum = Rl >= 0 ? -INFINITY : carry;   // sum of logsig(f~)
@@ -1075,7 +1082,7 @@ hipError_t launch_chunks(const ChunkKernelArgs& a, int S, hipStream_t stream) {
 
 template <LocalMode kMode>
 hipError_t launch_local(const LocalArgs& a, int S, hipStream_t stream) {
-    const size_t lds = sizeof(LocSmem<kMode == kRev ? 3 : 2>);
+    const size_t lds = sizeof(LocSmem<kLocalParts<kMode>>);
     static std::atomic<uint64_t> raised{0};
     auto kern = local_state_kernel<kMode>;
     hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kern), lds, raised);
