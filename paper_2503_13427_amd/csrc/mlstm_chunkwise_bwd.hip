@@ -345,7 +345,7 @@ __device__ __forceinline__ void dtile_update(DState& C, const uint16_t* Mt, cons
 }
 // The order of one dtile_update (half a chunk's) with its kTr transpose reads and kProducts products per pp: the
 // next chunk's load of a pp before its products, the operands one pp ahead.  Left to itself the compiler puts the
-// loads last, and the next chunk waits for them (x walk of 16 x 4096 tokens 854 us, 824 in this order).
+// loads last, and the next chunk waits for them (16 x 4096 tokens: x walk 854 us, 845 in this order; dk walk 820, 791).
 template <int kTr, int kProducts>
 __device__ __forceinline__ void dtile_update_order() {
     __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
@@ -870,7 +870,10 @@ __global__ void __launch_bounds__(256) bwd_rev_combine_kernel(float* seg, int NS
 // The weight g / den goes on Q, rounded once to bf16: dk sums Gam over v, so a rounding of a q element stays
 // a relative one of each term, where one of dH would be relative to dH's length in the product dH . V, which
 // is far smaller (the dv walk, which sums over d, puts it on dH for the same reason: on Q its largest row
-// error was 2.7 times as large).  gam's weights enter as three bf16 rows (24 bits).
+// error was 2.7 times as large).  Gam enters its product as a bf16 pair: c = k . dk and the reverse sums of r - c are
+// taken from the unrounded dk, and with Gam rounded once di~ was off by 7.5e-4 of its norm (5.3e-4 with the pair) and
+// df~ by 1.0e-2 (7.2e-3) at 1 x 2048 tokens; it costs 13 us of 760 at 16 x 4096.  gam's weights enter as three
+// bf16 rows (24 bits).
 struct DkSmem {
     uint16_t Ht[kDV * kTP];        // dH^T, rows in pair order
     uint16_t V[kBL * kRP];         // the chunk's V rows, then the exchange of the partial products
@@ -972,7 +975,7 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_dk_kernel(BwdParams A) {
         load(max(c - 1, c_begin), tid);
         __syncthreads();   // the chunk's operands are visible
         f32x4_t X[2][4];
-        dtile_product<false>(X, Gm, S.V, vq, lane, [&](int pp) {
+        dtile_product<true>(X, Gm, S.V, vq, lane, [&](int pp) {
             rh[2 * pp] = load_piece<8>(rdh, kDV * 2, tn, 2 * pp, wave, lane);
             rh[2 * pp + 1] = load_piece<8>(rdh, kDV * 2, tn, 2 * pp + 1, wave, lane);
         });
@@ -993,6 +996,7 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_dk_kernel(BwdParams A) {
             for (int dt = 0; dt < 2; ++dt) bw[0][dt] = tr_op(S.Q[1], kTP, 32 * ks, 32 * dp + 16 * dt, lane);
             dtile_update<1>(Gm, S.Ht, bw, vq, ks, lane,
                             [&](int i) { rvv[i] = load_row512(rv, tn, i, tid); });
+            dtile_update_order<4, 4>();
         }
         u32x4_t b[2][2];   // [ks][dt]: plain Q, the same way
 #pragma unroll
