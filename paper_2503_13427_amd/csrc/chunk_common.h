@@ -15,6 +15,7 @@ constexpr int kThreads = 512;
 constexpr int kWaves = 8;
 constexpr int kGateWave = kWaves - 1; // the wave with the least MFMA work runs the gate scans
 constexpr float kRenorm = -20.0f;     // rescale C eagerly when its lazy log-scale would drop below this
+constexpr float kRenormAlways = 1.0f; // a lazy log-scale is never positive
 
 // Chunks of 64 tokens; a call's own chunk length only shapes its segments (see launch_chunk_mfma).
 template <int L>
@@ -138,7 +139,7 @@ __device__ __forceinline__ void load_gates(float& gi, float& gf, const SeqRsrc& 
 // its entry state: C and n are scaled by zero before this chunk's keys are added.
 template <int L, bool kF32N>
 __device__ __forceinline__ void gate_phase(GateBuf<L, kF32N>& Gb, float gi, float gf, float& m_prev,
-                                           float& s_cur, int lane, int nvalid) {
+                                           float& s_cur, int lane, int nvalid, float renorm = kRenorm) {
     static_assert(L == 64, "one token per lane");
     const bool ok = lane < nvalid;
     const float lg = ok ? flogsig(gf) : 0.0f;
@@ -163,7 +164,7 @@ __device__ __forceinline__ void gate_phase(GateBuf<L, kF32N>& Gb, float gi, floa
     const bool empty = restart || (m_prev == -INFINITY);
     const float dlog = empty ? 0.0f : m_prev - ML;
     const float s_try = s_cur + dlog;
-    const bool eager = restart || s_try < kRenorm;
+    const bool eager = restart || s_try < renorm;
     const float s_new = eager ? 0.0f : s_try;
     auto emit = [&](int tau, float bb, float xx, float pp, float rr) {
         const bool fresh = (rr >= 0.0f);   // a restart at or before this row: no entry-state term

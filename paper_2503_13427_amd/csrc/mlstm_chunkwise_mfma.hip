@@ -180,6 +180,7 @@ struct ChunkKernelArgs {
     int R;             // local sub-segments per segment; segment g >= 1 enters from slot g R - 1
     int NS;            // local slots per sequence, (G - 1) R
     int seg_chunks;    // chunks per segment (last may be shorter)
+    int eager_chunk;   // a chunk whose state is rescaled eagerly (see launch_chunk_mfma), or -1
     uint16_t* h;
     float* CT;
     float* nT;
@@ -328,7 +329,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         load_qk<L>(rqk, P, t0, 0, tid, A.rq, A.rk);
         if (gate_wave) {
             load_gates<L>(gi, gf, P, t0, lane);
-            gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
+            gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0, c_begin == A.eager_chunk ? kRenormAlways : kRenorm);
         }
         store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
         load_v_tr<L>(rv, P, t0, v0, wave, lane, A.rv);
@@ -525,7 +526,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         // barrier, so the gate wave issues ahead of its SIMD partner meanwhile
         if (gate_wave && c + 1 < c_end) {
             __builtin_amdgcn_s_setprio(1);
-            gate_phase(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + L));
+            gate_phase(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + L), c + 1 == A.eager_chunk ? kRenormAlways : kRenorm);
             __builtin_amdgcn_s_setprio(0);
         }
 
@@ -1205,6 +1206,10 @@ hipError_t launch_chunk_mfma(const ChunkArgs& a, void* workspace, size_t workspa
     // tokens from a state against 1857 here, 452 against 405 for 16 x 2048, 18.7 against 17.4 for 100).  The
     // segments, and so the workspace, stay those of the caller's L.
     k.seg_chunks = sh.seg_chunks * (a.L / 64);
+    // A chunk that rescales C eagerly has weights exp(x - M_L), and the token with the largest is not rounded at
+    // all; with a lazy scale every term of C takes a rounding.  Chunks of 128 tokens rescaled about twice as often
+    // as their halves do, so for L = 128 the last chunk, which makes up most of the final state, always does.
+    k.eager_chunk = a.L == 128 ? (a.T + 63) / 64 - 1 : -1;
     k.h = static_cast<uint16_t*>(a.h);
     k.CT = a.CT;
     k.nT = a.nT;
