@@ -701,8 +701,10 @@ __global__ void __launch_bounds__(256, 2) bwd_intra_kernel(BwdParams A) {
     const float Dt = gt * qn + rsum;
     const float den = fmaxf(fabsf(Dt), flt);
     const bool act = fabsf(Dt) > flt;
-    const float rden = 1.0f / den;
-    const float gd = valid ? gt * rden : 0.0f;
+    // a row past the end has D = 0, and a floor that underflows once m exceeds 87: its 1 / den would be inf, and
+    // inf * 0 would enter the products over tau
+    const float rden = valid ? 1.0f / den : 0.0f;
+    const float gd = gt * rden;
     uint16_t* tSn = S.tile[wave][0];
     uint16_t* tPh = S.tile[wave][1];
     uint16_t* tPl = S.tile[wave][2];
