@@ -1277,12 +1277,14 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_dv_kernel(BwdParams A) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int sg = 16 * (2 * dh + i) + l16;
+            // rows past the end are dropped, all as row T: T may be up to 2^21 - 1, and the byte offset of an fp32
+            // row 2^21 is 2^32
+            const uint32_t row = static_cast<uint32_t>(min(t0 + sg, A.T));
             const float w = S.wk[sg];
 #pragma unroll
             for (int vt = 0; vt < 2; ++vt) {
                 const f32x4_t y = X[vt][i] + S.ex[wave ^ 1][2 * i + vt][lane];
-                store_grad<kBf16>(rdv, static_cast<uint32_t>(t0 + sg) * kDV + v0 + 32 * vq + 16 * vt + 4 * g16,
-                                  w * y + in[i][vt]);
+                store_grad<kBf16>(rdv, row * kDV + v0 + 32 * vq + 16 * vt + 4 * g16, w * y + in[i][vt]);
             }
         }
     }
