@@ -524,8 +524,24 @@ __global__ void __launch_bounds__(64 * kMmaW) chunk_f32_mma_kernel(F32Args A) {
                 for (int w = 0; w < kMmaW; ++w) sum += Np[(w * L + t) * 16 + l16];
                 acc[i] = static_cast<double>(g_inter[t]) * qscale * sum;
             }
-            for (int s4 = 0; s4 < 16 * (nt + 1); s4 += 4)
+            for (int s4 = 0; s4 < 16 * nt; s4 += 4)
                 acc = mfma_f64(Sm[(16 * nt + l16) * SP + s4 + g], Vs[(s4 + g) * kMmaVP + l16], acc);
+            float vd[4];   // the diagonal tile, zero in S above the diagonal
+            bool finite = true;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                vd[i] = Vs[(16 * nt + 4 * i + g) * kMmaVP + l16];
+                finite = finite && fabsf(vd[i]) < INFINITY;
+            }
+            if (__builtin_amdgcn_ballot_w64(finite) == ~uint64_t{0}) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc = mfma_f64(Sm[(16 * nt + l16) * SP + 16 * nt + 4 * i + g], vd[i], acc);
+            } else {   // zero times inf or NaN would reach the tokens before it: only the terms s <= t
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    for (int r = 0; r <= 4 * i + g; ++r)
+                        acc[i] += static_cast<double>(Sm[(16 * nt + 4 * i + g) * SP + 16 * nt + r]) * Vs[(16 * nt + r) * kMmaVP + l16];
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int t = 16 * nt + 4 * i + g;

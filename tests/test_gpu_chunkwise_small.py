@@ -142,3 +142,19 @@ def test_fp32_kernels_match_oracle(T, DQK, DV, L, dt):
     inp.fpre[:, 1, T - 1] = -np.inf
     out = run_chunk(inp, L)
     compare(inp, out, TOL_F32 if dt == "f32" else TOL_BF16)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("L", [16, 32, 64])
+def test_fp32_kernel_is_causal_in_non_finite_values(L, bad):
+    """A value of inf or NaN does not reach the outputs of the tokens before it."""
+    T, at = 70, 41
+    inp = make_prefill(workload=92, B=1, NH=2, T=T, DQK=32, DV=32, dtype="f32", gates=GateDist(), state=StateDist(),
+                       k_scale=1 / np.sqrt(32))
+    ref = run_chunk(inp, L)["h"].reshape(2, T, 32)
+    inp.v[:, :, at] = bad
+    h = run_chunk(inp, L)["h"].reshape(2, T, 32)
+    assert np.isfinite(h[:, :at]).all() and not np.isfinite(h[:, at:]).any()
+    assert np.array_equal(h[:, :at - at % 16], ref[:, :at - at % 16])
+    # the bad value's own tile of 16 tokens is summed in another order
+    assert np.abs(h[:, :at] - ref[:, :at]).max() <= 1e-6 * np.abs(ref).max()
