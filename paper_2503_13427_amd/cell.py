@@ -52,12 +52,12 @@ class _MLSTMCell(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dh, _dCT, _dnT, _dmT):
-        if dh is None:
-            return (None,) * 9
         q, k, v, ipre, fpre, C0, n0, m0 = ctx.saved_tensors
         B, NH, T, DQK = q.shape
         DV = v.shape[3]
         dev = q.device
+        if dh is None:   # nothing reached h: zero gradients, not undefined ones
+            dh = torch.zeros(B, NH, T, DV, dtype=q.dtype, device=dev)
         # the chunkwise backward rounds dq, dk, dv to their dtype itself; the parallel form's are fp32
         dt = q.dtype if ctx.chunkwise else torch.float32
         dq = torch.empty(B, NH, T, DQK, dtype=dt, device=dev)
