@@ -290,9 +290,10 @@ def mlstm_chunkwise_bwd(q, k, v, ipre, fpre, C0, n0, m0, L, dh, dq, dk, dv, dipr
     B, NH, T, DQK = q.shape
     DV = v.shape[3]
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    if not dq.dtype == dk.dtype == dv.dtype:
-        raise TypeError(f"dq, dk and dv must have one dtype, got {dq.dtype}, {dk.dtype}, {dv.dtype}")
-    bwd = lib.mlstm_chunkwise_bwd_rounded if dq.dtype == torch.bfloat16 else lib.mlstm_chunkwise_bwd
+    grads = {g.dtype for g in (dq, dk, dv) if g is not None}   # a None is the library's to refuse
+    if torch.bfloat16 in grads and len(grads) > 1:
+        raise TypeError(f"dq, dk and dv must have one dtype, got {grads}")
+    bwd = lib.mlstm_chunkwise_bwd_rounded if torch.bfloat16 in grads else lib.mlstm_chunkwise_bwd
     _check(bwd(_ptr(q), _ptr(k), _ptr(v), _dtype_code(q), _ptr(ipre), _ptr(fpre), _ptr(C0), _ptr(n0), _ptr(m0), B, NH, T,
                DQK, DV, L, _ptr(dh), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dipre), _ptr(dfpre), _ptr(dC0), _ptr(dn0),
                _ptr(dm0), _ptr(workspace), ws_bytes, _stream(stream)))

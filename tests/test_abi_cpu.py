@@ -601,3 +601,19 @@ def test_chunk_bwd_alias(out, other, off):
 def test_chunk_bwd_state_gradient_alias():
     a = cbwd_args(C0=fake(13), n0=fake(14), m0=fake(15), dC0=fake(13, 64), dn0=fake(16), dm0=fake(17))
     assert call_cbwd(a) == 5
+
+
+def test_binding_leaves_missing_gradients_to_the_library():
+    """A gradient that is None is an error with a token, and nothing without one, as in the C call."""
+    def args(T, dq=None):
+        bf, f32 = dict(dtype=torch.bfloat16), dict(dtype=torch.float32)
+        e = torch.empty
+        return [e(1, 1, T, 256, **bf), e(1, 1, T, 256, **bf), e(1, 1, T, 512, **bf), e(1, 1, T, **f32), e(1, 1, T, **f32),
+                None, None, None, 64, e(1, 1, T, 512, **bf), dq, e(1, 1, T, 256), e(1, 1, T, 512), e(1, 1, T), e(1, 1, T),
+                None, None, None, None]
+    with pytest.raises(Bd.MlstmError) as err:
+        Bd.mlstm_chunkwise_bwd(*args(1), stream=0)
+    assert err.value.status == 1
+    Bd.mlstm_chunkwise_bwd(*args(0), stream=0)
+    with pytest.raises(TypeError):
+        Bd.mlstm_chunkwise_bwd(*args(1, torch.empty(1, 1, 1, 256, dtype=torch.bfloat16)), stream=0)
