@@ -12,7 +12,8 @@ stream: ``ms_per_step`` is the mean over the K timed calls, and the median,
 p10 and p90 of the per-call times are reported beside it.
 
 Extra objects on the same line:
-  roofline      achieved bf16 TFLOP/s (App. D.1 FLOP count per call / mean call
+  roofline      achieved bf16 TFLOP/s (App. D.1 FLOP count per call, in the chunks of
+                64 tokens that the call runs / mean call
                 duration) vs 2.5 PFLOP/s, and the HBM bytes per call from the
                 committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary;
   cpu_baseline  the fp64 CPU oracle on a sample of the same workload (host
@@ -73,6 +74,14 @@ def dev(x, device="cuda"):
     return t.to(device)
 
 
+PREFILL_CHUNK = 64   # tokens per chunk that the bf16 prefill runs, for L = 128 calls too
+
+
+def prefill_flops(w):
+    """App. D.1's count of one call, in the chunks that it runs: L = 128 would count products that no kernel does."""
+    return acc.flops_chunkwise(w.B * w.NH, w.T, min(w.L, PREFILL_CHUNK), w.DQK, w.DV).total
+
+
 class Prefill:
     """Device buffers for one prefill workload, NINPUT rotated input copies."""
 
@@ -101,8 +110,7 @@ class Prefill:
                                     self.h, self.CT, self.nT, self.mT, workspace=self.ws, stream=stream)
 
     def flops(self):
-        w = self.w
-        return acc.flops_chunkwise(w.B * w.NH, w.T, w.L, w.DQK, w.DV).total
+        return prefill_flops(self.w)
 
     def bytes(self):
         w = self.w
@@ -385,7 +393,7 @@ def bench_layer_prefill(layer, B, T, steps, stream):
     t_out = run(lambda: torch.matmul(yh.view(B * T, NH * DV), w.W_proj))
     tok = B * T
     fl_proj = acc.flops_layer_projections(tok, d, NH, DQK, DV)
-    fl_cell = acc.flops_chunkwise(B * NH, T, layer.L, DQK, DV).total
+    fl_cell = acc.flops_chunkwise(B * NH, T, min(layer.L, PREFILL_CHUNK), DQK, DV).total
     stages = dict(projections=t_proj, gates=t_gates, cell=t_cell, output_norm=t_norm, output_projection=t_out)
     return dict(workload=f"layer_prefill_B{B}_T{T}_d{d}_NH{NH}", B=B, T=T, tokens_per_s=tok / t_total,
                 ms_per_call=t_total * 1e3, tflops=(fl_proj + fl_cell) / t_total / 1e12,

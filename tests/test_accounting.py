@@ -58,3 +58,12 @@ def test_layer_step_bytes():
     assert A.layer_weight_bytes(d, NH, dqk, dv) == 2 * bf16_params + 4 * f32_params
     state = A.state_bytes(1, NH, dqk, dv) + 4 * NH * (dqk + 1)
     assert A.layer_step_bytes(1, d, NH, dqk, dv) == 2 * bf16_params + 4 * f32_params + 2 * state + 4 * d
+
+
+def test_prefill_utilisation_counts_the_chunks_that_run():
+    """The bf16 prefill walks chunks of 64 tokens for L = 128 calls too, so that is what its FLOP rate counts."""
+    import bench
+    from paper_2503_13427_amd import configs
+    w = configs.CONT_PREFILL_T32768
+    assert w.L == 128
+    assert bench.prefill_flops(w) == A.flops_chunkwise(32, 32768, 64, 256, 512).total
