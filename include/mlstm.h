@@ -328,9 +328,10 @@ mlstm_status mlstm_parallel_bwd(const void* q, const void* k, const void* v, mls
  * restart that recurrence as in the forward.  The forward's output is not
  * needed: dh . h~ is formed from the recomputed numerator in fp32.  Products
  * run on bf16 MFMA with fp32 accumulation; the recomputed states enter them
- * as bf16 hi + lo pairs, the carried state gradients (accumulated in fp32)
- * rounded once to bf16.  No float atomics: the
- * result is deterministic.
+ * as bf16 hi + lo pairs, and so do the carried state gradients (accumulated
+ * in fp32) for dk, while dv takes them rounded once to bf16.  No float
+ * atomics: the result is deterministic.  The gradient jumps where the
+ * denominator's |D_t| meets its floor; the branch is decided in fp32.
  *
  *   q, k [B, NH, T, DQK], v [B, NH, T, DV] (dt)   ipre, fpre [B, NH, T] fp32
  *   C0 [B, NH, DQK, DV], n0 [B, NH, DQK], m0 [B, NH] fp32: the forward's

@@ -1356,7 +1356,8 @@ size_t align256(size_t b) { return (b + 255) & ~static_cast<size_t>(255); }
 
 // The workspace size callers are told (mlstm_chunkwise_bwd_workspace_bytes), a fixed formula of the
 // interface: per sequence and chunk but the first a state slot and a bf16 state matrix, the segment slots,
-// four fp32 copies of q, and per-token terms.  The passes below use about an eighth of it.
+// four fp32 copies of q, and per-token terms.  The passes below use about an eighth of it (94 KB of 1 MB per
+// chunk, and the segment slots).
 size_t published_workspace_bytes(int64_t S, int T) {
     const int64_t NC = (T + kBL - 1) / kBL, NC1 = NC > 0 ? NC - 1 : 0;
     return align256(static_cast<size_t>(S * NC1 * kSlotFloats) * 4) +
@@ -1368,7 +1369,7 @@ size_t published_workspace_bytes(int64_t S, int T) {
 }
 
 // Lays the arrays of the passes out in the workspace; returns the bytes used.  A chunk of 64 tokens
-// takes 64 KB of X, 24 KB of St and P and about 10 KB of scalars and states, under the 256 KB of the four
+// takes 64 KB of X, 24 KB of St and P and about 6 KB of scalars and states, under the 256 KB of the four
 // copies of q that the published size counts for a full chunk; what rounding a partial chunk up to 64
 // tokens adds is under the 513 KB it counts once per sequence.
 size_t lay_out(BwdParams& p, unsigned char* ws) {

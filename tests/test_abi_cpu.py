@@ -544,11 +544,10 @@ def call_cbwd(a, entry):
 
 
 def test_chunk_bwd_workspace_size():
-    """Slots of every chunk but the first (n, m, then L_c, z_c); the segment slots of the walk (32
-    sequence-tile workgroups per segment, so eight segments of four chunks: seven segment slots per
-    sequence); the four dv tiles' partial sums of X; Gam_c in bf16; L_0, gam per chunk,
-    per-token key weights and partial sums, per-chunk decays, dm0 partial sums; each region 256-byte
-    aligned."""
+    """The size that the interface fixes, each region 256-byte aligned: per sequence and chunk but the first a state
+    slot and a bf16 state matrix; the segment slots (32 sequence-tile workgroups per segment, so eight segments
+    of four chunks: seven segment slots per sequence); four fp32 copies of q; one state; per-chunk vectors,
+    per-token and per-chunk terms, partial sums.  The passes lay their own arrays out within it."""
     al = lambda b: (b + 255) // 256 * 256
     S, T, NC = 8, 2048, 32
     slot = 256 * 512 + 256 + 4
