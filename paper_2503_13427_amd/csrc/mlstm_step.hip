@@ -263,27 +263,33 @@ step_kernel(const TIn* __restrict__ q, const TIn* __restrict__ k, const TIn* __r
     if (write_nm && tid == 0) m_out[head] = mnew;
 }
 
-// The split launch's second kernel, one workgroup of two waves per sequence (one launch for both: a decode
-// step at batch 1 is a chain of launches).  The first wave writes n' = f n + i k and m'; with an output
-// epilogue (E.o) the second takes the gated norm of the row h~ that the first kernel's workgroups have put
-// together in h, in place, from registers.  Every element of n and of h is read and written by one lane, and m
-// is read only by the wave that writes it, so n_out and m_out may be n and m; the waves share nothing and
-// there is no barrier (as four waves per row with two block reductions it took 4.6 us instead of 3.6).
+// The split launch's second kernel, one workgroup per sequence (one launch for all of it: a decode
+// step at batch 1 is a chain of launches).  All waves but the last write n' = f n + i k, a round of 4 x 64 elements
+// per wave at a time, and the first one m'; with an output
+// epilogue (E.o) the last wave takes the gated norm of the row h~ that the first kernel's workgroups have put
+// together in h, in place, from registers.  Every element of n and of h is read and written by one lane.  With one
+// wave for n (DQK <= 256) m is read only by the wave that writes it, the waves share nothing and
+// there is no barrier (as four waves per row with two block reductions it took 4.6 us instead of 3.6); with more
+// the barrier puts every read of m before its write.  Either way n_out and m_out may be n and m.
 constexpr int kFinishPer = kOutPerThread * kStepThreads / 256;   // groups of four row elements per lane at most
+// Waves for n: a wave takes about 0.6 us per round (one wave for all of n took 13.0 us for DQK = 4096 and 6.4 for
+// 1024, where four waves take 4.0 and 4.6).
+constexpr int finish_n_waves(int DQK) { return DQK <= 256 ? 1 : DQK <= 512 ? 2 : 4; }
 template <typename TIn>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(320)
 step_finish_kernel(const TIn* __restrict__ k, const float* __restrict__ ipre, const float* __restrict__ fpre,
                    const float* n, const float* m, int DQK, int DV, TIn* h, float* n_out, float* m_out, StepOut<TIn> E) {
     const int64_t head = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nw = finish_n_waves(DQK);
+    if (wave < nw) {
         const float mprev = m[head];
         const float a = logsigmoid(fpre[head]);
         const float it = ipre[head];
         const float mnew = fmaxf(a + mprev, it);
         const float fg = expf(a + mprev - mnew);
         const float ig = expf(it - mnew);
-        for (int d0 = 0; d0 < DQK; d0 += 4 * 64) {
+        for (int d0 = 256 * wave; d0 < DQK; d0 += 256 * nw) {
             float nv[4], kv[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -297,9 +303,11 @@ step_finish_kernel(const TIn* __restrict__ k, const float* __restrict__ ipre, co
                 if (d < DQK) n_out[head * DQK + d] = fg * nv[u] + ig * kv[u];
             }
         }
-        if (lane == 0) m_out[head] = mnew;
+        if (nw > 1) __syncthreads();
+        if (threadIdx.x == 0) m_out[head] = mnew;
         return;
     }
+    if (nw > 1) __syncthreads();
     if (!E.o) return;
     const int64_t hd = static_cast<int64_t>(head % E.NH) * DV;
     float hv[kFinishPer][4], ov[kFinishPer][4], wv[kFinishPer][4], bv[kFinishPer][4];
@@ -362,7 +370,7 @@ static hipError_t launch_step_t(const void* q, const void* k, const void* v, con
                        static_cast<const TIn*>(k), static_cast<const TIn*>(v), ipre, fpre, C, n, m, DQK, DV, P,
                        static_cast<TIn*>(h), C_out, n_out, m_out, P > 1 ? StepOut<TIn>{} : E);
     if (P > 1)
-        hipLaunchKernelGGL(step_finish_kernel<TIn>, dim3(heads), dim3(128), 0, stream,
+        hipLaunchKernelGGL(step_finish_kernel<TIn>, dim3(heads), dim3(64 * (finish_n_waves(DQK) + (E.o ? 1 : 0))), 0, stream,
                            static_cast<const TIn*>(k), ipre, fpre, n, m, DQK, DV, static_cast<TIn*>(h), n_out, m_out, E);
     return hipGetLastError();
 }

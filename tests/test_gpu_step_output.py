@@ -40,6 +40,10 @@ CASES = [
     (300, 1, 64, 128, "f32", "layer", True, 3),     # fp32, fused
     (2, 2, 16, 32, "f32", "rms", True, 2),          # fp32, few sequences
     (1, 4, 32, 2048, "f32", "layer", False, 2),     # the widest row the output takes
+    # few sequences, n over several waves: two, the last of its four rounds partial; four, one and four rounds
+    (1, 2, 257, 64, "f32", "layer", True, 3),
+    (2, 1, 516, 96, "bf16", "rms", True, 2),
+    (1, 2, 4096, 64, "f32", "layer", True, 2),
 ]
 
 
