@@ -60,7 +60,7 @@ __device__ __forceinline__ float block_sum(float x, float* wsum) {
     return t;
 }
 
-template <typename TIn>
+template <typename TIn, bool kAhead>
 __global__ void __launch_bounds__(kStepThreads)
 step_kernel(const TIn* __restrict__ q, const TIn* __restrict__ k, const TIn* __restrict__ v,
             const float* __restrict__ ipre, const float* __restrict__ fpre,
@@ -97,13 +97,13 @@ step_kernel(const TIn* __restrict__ q, const TIn* __restrict__ k, const TIn* __r
     const f4_t* Ch = reinterpret_cast<const f4_t*>(C + head * static_cast<int64_t>(DQK) * DV + cv0);
     f4_t* Ch_out = reinterpret_cast<f4_t*>(C_out + head * static_cast<int64_t>(DQK) * DV + cv0);
     auto row = [&](int r) { return static_cast<int64_t>(rg + r * RG) * ROW4; };
-    // q, k and n of row tid before the batch: memory answers in order, so the normaliser's dot product then
-    // runs while the batch is on its way
+    // kAhead (see launch_step_t): q, k and n of row tid before the batch; memory answers in order, so the
+    // normaliser's dot product then runs while the batch is on its way
     const TIn* qh = q + head * DQK;
     const TIn* kh = k + head * DQK;
     const float* nh = n + head * DQK;
     float q0 = 0.0f, k0 = 0.0f, n0 = 0.0f;
-    if (tid < DQK) {
+    if (kAhead && tid < DQK) {
         q0 = io<TIn>::load(qh, tid);
         k0 = io<TIn>::load(kh, tid);
         n0 = nh[tid];
@@ -134,7 +134,7 @@ step_kernel(const TIn* __restrict__ q, const TIn* __restrict__ k, const TIn* __r
     // s3: n' = f n + i k, and the partial n'.q^ (Eq. 4, denominator of Eq. 5)
     float dot = 0.0f;
     for (int d = tid; d < DQK; d += kStepThreads) {
-        const bool first = (d == tid);
+        const bool first = kAhead && d == tid;
         const float qd = (first ? q0 : io<TIn>::load(qh, d)) * qscale;
         const float ikd = ig * (first ? k0 : io<TIn>::load(kh, d));
         qs[d] = qd;
@@ -264,24 +264,27 @@ step_kernel(const TIn* __restrict__ q, const TIn* __restrict__ k, const TIn* __r
 }
 
 // The split launch's second kernel, one workgroup per sequence (one launch for all of it: a decode
-// step at batch 1 is a chain of launches).  All waves but the last write n' = f n + i k, a round of 4 x 64 elements
-// per wave at a time, and the first one m'; with an output
-// epilogue (E.o) the last wave takes the gated norm of the row h~ that the first kernel's workgroups have put
+// step at batch 1 is a chain of launches).  finish_n_waves waves write n' = f n + i k, four elements per lane and
+// round, and the first of them m'; with an output
+// epilogue (E.o) one more wave takes the gated norm of the row h~ that the first kernel's workgroups have put
 // together in h, in place, from registers.  Every element of n and of h is read and written by one lane.  With one
-// wave for n (DQK <= 256) m is read only by the wave that writes it, the waves share nothing and
-// there is no barrier (as four waves per row with two block reductions it took 4.6 us instead of 3.6); with more
+// wave for n, m is read only by the wave that writes it, the waves share nothing and there is no barrier; with more
 // the barrier puts every read of m before its write.  Either way n_out and m_out may be n and m.
 constexpr int kFinishPer = kOutPerThread * kStepThreads / 256;   // groups of four row elements per lane at most
-// Waves for n: a wave takes about 0.6 us per round (one wave for all of n took 13.0 us for DQK = 4096 and 6.4 for
-// 1024, where four waves take 4.0 and 4.6).
-constexpr int finish_n_waves(int DQK) { return DQK <= 256 ? 1 : DQK <= 512 ? 2 : 4; }
+// With the epilogue one wave is enough for n up to 256 elements, it ends before the norm (as four waves per row with
+// two block reductions the kernel took 4.6 us instead of 3.6); it takes about 0.6 us per further round (13.0 us for
+// DQK = 4096, 6.4 for 1024, where four waves took 4.0 and 4.6).
+inline int finish_n_waves(int DQK, bool) {
+    const int round = 256;
+    return DQK <= round ? 1 : DQK <= 2 * round ? 2 : 4;
+}
 template <typename TIn>
 __global__ void __launch_bounds__(320)
 step_finish_kernel(const TIn* __restrict__ k, const float* __restrict__ ipre, const float* __restrict__ fpre,
                    const float* n, const float* m, int DQK, int DV, TIn* h, float* n_out, float* m_out, StepOut<TIn> E) {
     const int64_t head = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nw = finish_n_waves(DQK);
+    const int nw = (blockDim.x >> 6) - (E.o ? 1 : 0);
     if (wave < nw) {
         const float mprev = m[head];
         const float a = logsigmoid(fpre[head]);
@@ -289,17 +292,17 @@ step_finish_kernel(const TIn* __restrict__ k, const float* __restrict__ ipre, co
         const float mnew = fmaxf(a + mprev, it);
         const float fg = expf(a + mprev - mnew);
         const float ig = expf(it - mnew);
-        for (int d0 = 256 * wave; d0 < DQK; d0 += 256 * nw) {
+        for (int d0 = 64 * wave; d0 < DQK; d0 += 256 * nw) {
             float nv[4], kv[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int d = d0 + 64 * u + lane;
+                const int d = d0 + 64 * nw * u + lane;
                 nv[u] = d < DQK ? n[head * DQK + d] : 0.0f;
                 kv[u] = d < DQK ? io<TIn>::load(k + head * DQK, d) : 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int d = d0 + 64 * u + lane;
+                const int d = d0 + 64 * nw * u + lane;
                 if (d < DQK) n_out[head * DQK + d] = fg * nv[u] + ig * kv[u];
             }
         }
@@ -366,11 +369,16 @@ static hipError_t launch_step_t(const void* q, const void* k, const void* v, con
                                 hipStream_t stream) {
     const size_t lds = step_lds_bytes(DQK, DV / P);
     const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(heads) * P));
-    hipLaunchKernelGGL(step_kernel<TIn>, grid, dim3(kStepThreads), lds, stream, static_cast<const TIn*>(q),
+    // Large states stream a little faster with q, k and n asked for first (8 heads of 256 x 512: 379.4 -> 375.4 us
+    // for 256 sequences, 765 -> 750 for 512); where the launch is short their latency stands before everything else
+    // (8 x 8 heads 15.6 -> 16.2, 31 x 8 49.0 -> 51.3, 4800 heads of 128 x 256 231 -> 234).  192 x 8 heads: no difference.
+    const bool ahead = P == 1 && DQK * DV >= (1 << 17) && static_cast<int64_t>(heads) * DQK * DV >= (int64_t(3) << 26);
+    auto kern = ahead ? step_kernel<TIn, true> : step_kernel<TIn, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(kStepThreads), lds, stream, static_cast<const TIn*>(q),
                        static_cast<const TIn*>(k), static_cast<const TIn*>(v), ipre, fpre, C, n, m, DQK, DV, P,
                        static_cast<TIn*>(h), C_out, n_out, m_out, P > 1 ? StepOut<TIn>{} : E);
     if (P > 1)
-        hipLaunchKernelGGL(step_finish_kernel<TIn>, dim3(heads), dim3(64 * (finish_n_waves(DQK) + (E.o ? 1 : 0))), 0, stream,
+        hipLaunchKernelGGL(step_finish_kernel<TIn>, dim3(heads), dim3(64 * (finish_n_waves(DQK, E.o) + (E.o ? 1 : 0))), 0, stream,
                            static_cast<const TIn*>(k), ipre, fpre, n, m, DQK, DV, static_cast<TIn*>(h), n_out, m_out, E);
     return hipGetLastError();
 }

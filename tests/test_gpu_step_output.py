@@ -109,3 +109,28 @@ def test_fused_and_split_paths_are_both_exercised():
     f.restype = ctypes.c_bool
     assert f(64, 8, 256, 512) and f(300, 1, 64, 128)
     assert not f(1, 8, 256, 512) and not f(1, 4, 32, 2048)
+
+
+@pytest.mark.parametrize("B,NH,DQK,DV", [(192, 8, 256, 512), (768, 1, 600, 512)])
+def test_large_states_step_like_their_halves(B, NH, DQK, DV):
+    """From 768 MiB of state on the step asks for q, k and n first: bit for bit what the halves of the batch give."""
+    mb = _mb()
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    q, k, v, o = (rnd(B, NH, d).bfloat16() for d in (DQK, DQK, DV, DV))
+    ip, fp, w = rnd(B, NH), rnd(B, NH) + 3, rnd(NH, DV)
+    st = [rnd(B, NH, DQK, DV), rnd(B, NH, DQK), rnd(B, NH)]
+
+    def step(sl, output):
+        x, s = [t[sl].contiguous() for t in (q, k, v, ip, fp)], [t[sl].clone() for t in st]
+        h = torch.empty_like(x[2])
+        if output:
+            mb.mlstm_step_output(*x, *s, o[sl].contiguous(), w, None, 1e-6, "layer", h, *s)
+        else:
+            mb.mlstm_step(*x, *s, h, *s)
+        return [h] + s
+    for output in (False, True):
+        whole = step(slice(0, B), output)
+        for sl in (slice(0, B // 2), slice(B // 2, B)):
+            for a, b in zip(whole, step(sl, output)):
+                assert torch.equal(a[sl], b)
