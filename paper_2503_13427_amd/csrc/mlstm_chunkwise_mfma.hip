@@ -203,9 +203,10 @@ static_assert(kDQK * kStageP * 4 <= sizeof(Smem<64>), "staging");
 // block p is requested after block p's logits, its V during block 0's read-out; V is transposed in registers
 // at the barrier that opens block 1, its weighted copy goes to LDS after the S~ barrier (once this chunk's
 // (iv) is done and the next chunk's weights are known), its plain copy at the top of the next chunk (once
-// this chunk's (ii) is done).  All of it runs in every chunk (the last one repeats its own loads): behind a
+// this chunk's (ii) is done).  The loads run in every chunk (the last one repeats its own): behind a
 // branch the compiler cannot count the loads in flight and waits for all of them, and a harmless change of
 // the code around has moved such a wait right behind the loads (950 instead of 795 us for 8 x 8192 tokens).
+// What the loads feed is left out in the last chunk (with it, calls of one chunk took 13.4 instead of 13.0 us).
 template <int L>
 __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -391,8 +392,10 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
             if (p > 0) {
                 __syncthreads();   // block p visible, block p - 1 fully read
                 // block 0 of the next chunk; its V, transposed in registers
-                store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
-                vt_transpose<L>(pv, rv, lane);
+                if (c + 1 < c_end) {
+                    store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
+                    vt_transpose<L>(pv, rv, lane);
+                }
             }
             // (i) S^T += K_p Q_p^T on this wave's causal tiles
 #pragma unroll
@@ -591,7 +594,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         __syncthreads();
         // the next chunk's scaled V^T (its readers, (iv) of this chunk, are done; the next chunk's
         // weights are visible)
-        vt_store_scaled<L>(S.Vs[1], pv, S.G[par ^ 1].wC, wave, lane);
+        if (c + 1 < c_end) vt_store_scaled<L>(S.Vs[1], pv, S.G[par ^ 1].wC, wave, lane);
         // (ii) N^T = interC * N^T + V^T S~^T, then h = N^T / max(|den|, floor); each
         // d partition finishes the tau tiles T with T % 2 == dh, after adding the other's partial
 #pragma unroll
