@@ -17,8 +17,8 @@ constexpr int kGateWave = kWaves - 1; // the wave with the least MFMA work runs 
 constexpr float kRenorm = -20.0f;     // rescale C eagerly when its lazy log-scale would drop below this
 constexpr float kRenormAlways = 1.0f; // a lazy log-scale is never positive
 
-// Chunks of 64 tokens; a call's own chunk length only shapes its segments (see launch_chunk_mfma).
-template <int L>
+// Tokens per chunk; a call's own chunk length only shapes its segments (see launch_chunk_mfma).
+constexpr int kL = 64;
 struct Cfg {
     static constexpr int NDB = 2;                   // d blocks staged per chunk
     static constexpr int DB = kDQK / NDB;           // 128
@@ -26,8 +26,8 @@ struct Cfg {
     // row pitch (elements) of Q and K blocks: 288 bytes keep the 16-byte row reads of 16 consecutive rows
     // free of bank conflicts
     static constexpr int QP = DB + 16;
-    static constexpr int SP = L + 16;               // row pitch of S~ (160 bytes)
-    static constexpr int QKE = L * QP;              // elements of one Q or K block buffer
+    static constexpr int SP = kL + 16;               // row pitch of S~ (160 bytes)
+    static constexpr int QKE = kL * QP;              // elements of one Q or K block buffer
     // Wave split of the workgroup's 256 x 128 slice of C: DH d partitions x (8 / DH) column
     // groups of VT 16-column tiles.  Two partitions halve the Q and K^T operand reads of
     // (iii) and (iv) at the price of summing the two partial read-outs of (iii) through LDS.
@@ -36,27 +36,26 @@ struct Cfg {
     static constexpr int NVG = kWaves / DH;
     // V is kept in LDS transposed (rows v, tau contiguous, pitch TP), once plain for (ii) and once
     // scaled by the C-update key weights for (iv), so both read it with plain 16-byte row reads
-    static constexpr int TP = L + 8;
+    static constexpr int TP = kL + 8;
 };
 
 // Per-chunk gate quantities, written one chunk ahead by the gate wave.  kF32N: the n-update weights in fp32, for
 // the backward, which branches on |q . n + ...| against the floor, so that n's rounding decides rows close to it.
-template <int L, bool kF32N = false>
+template <bool kF32N>
 struct alignas(16) GateBuf {
-    float x2[L];        // (i~ - b) * log2 e
-    float M2[L];        // M * log2 e (0 for a row with no input at all)
-    int R[L];           // last restart (forget gate exactly zero) at or before the row, -1: none
-    float interC[L];    // exp(m_prev - M + s) / sqrt(DQK): scale of C_acc^T Q^T
-    float interN[L];    // exp(m_prev - M) / sqrt(DQK):     scale of Q n
-    float floorv[L];    // exp(-(b + M))
-    float wC[L];        // C-update weights exp(x - M_L - s_new)
-    std::conditional_t<kF32N, float[L], uint16_t[2][L]> wb;   // n-update weights exp(x - M_L): fp32, or bf16 hi / lo rows
+    float x2[kL];        // (i~ - b) * log2 e
+    float M2[kL];        // M * log2 e (0 for a row with no input at all)
+    int R[kL];           // last restart (forget gate exactly zero) at or before the row, -1: none
+    float interC[kL];    // exp(m_prev - M + s) / sqrt(DQK): scale of C_acc^T Q^T
+    float interN[kL];    // exp(m_prev - M) / sqrt(DQK):     scale of Q n
+    float floorv[kL];    // exp(-(b + M))
+    float wC[kL];        // C-update weights exp(x - M_L - s_new)
+    std::conditional_t<kF32N, float[kL], uint16_t[2][kL]> wb;   // n-update weights exp(x - M_L): fp32, or bf16 hi / lo rows
     float scal[4];      // [0] n decay, [1] m_next, [2] s_new, [3] eager C scale (1: none)
 };
 
-template <int L>
 struct VRegs {
-    static constexpr int N = (L * kDVT / 8) / kThreads;   // 16-byte pieces of a V chunk per thread
+    static constexpr int N = (kL * kDVT / 8) / kThreads;   // 16-byte pieces of a V chunk per thread
     u32x4_t v[N];
 };
 
@@ -64,22 +63,19 @@ struct VRegs {
 // V[tau 16 a + l16][v 32 b + 8 g16 + 0..7], (a, b) = (w % 4, N (w / 4) + i); the workgroup's pieces cover
 // the 64 x 128 chunk once, and a wave's pieces are neighbours in v, so that the two 64-byte halves of a
 // memory line are requested one after the other.
-template <int L>
-__device__ __forceinline__ int v_piece_b(int wave, int i) { return VRegs<L>::N * (wave >> 2) + i; }
-template <int L>
-__device__ __forceinline__ void load_v_tr(VRegs<L>& r, const SeqRsrc& R, int t0, int v0, int wave, int lane, uint32_t rv) {
-    static_assert(L == 64 && VRegs<L>::N * kWaves == (L / 16) * (kDVT / 32), "pieces of one 64 x 128 chunk");
+__device__ __forceinline__ int v_piece_b(int wave, int i) { return VRegs::N * (wave >> 2) + i; }
+__device__ __forceinline__ void load_v_tr(VRegs& r, const SeqRsrc& R, int t0, int v0, int wave, int lane, uint32_t rv) {
+    static_assert(VRegs::N * kWaves == (kL / 16) * (kDVT / 32), "pieces of one 64 x 128 chunk");
     const uint32_t soff = v0 * 2;   // the row offset goes in the per-lane offset
     int ln = lane;   // opaque: the offsets are recomputed per call rather than held across the loop
     asm volatile("" : "+v"(ln));
 #pragma unroll
-    for (int i = 0; i < VRegs<L>::N; ++i) {
-        const int a = wave & 3, b = v_piece_b<L>(wave, i);
+    for (int i = 0; i < VRegs::N; ++i) {
+        const int a = wave & 3, b = v_piece_b(wave, i);
         r.v[i] = bload128(R.v, static_cast<uint32_t>(t0 + 16 * a + (ln & 15)) * rv + (32 * b + 8 * (ln >> 4)) * 2, soff);
     }
 }
-template <int L>
-using VtPacked = u32x2_t[2 * VRegs<L>::N];
+using VtPacked = u32x2_t[2 * VRegs::N];
 // The transposition on the matrix cores: D = A E_h with A a piece (16 tau x 32 v) and E_h the 32 x 16
 // one-hot selection of its columns 16 h + 0..15 (exact in fp32).  Lane (n = l16, g16) of D holds
 // V[tau 16 a + 4 g16 + j][v 32 b + 16 h + n], j = 0..3: four consecutive tau of one row of V^T, kept
@@ -104,12 +100,11 @@ __device__ __forceinline__ void onehot_pair(u32x4_t (&E)[2], int lane) {
     }
 }
 
-template <int L>
-__device__ __forceinline__ void vt_transpose(VtPacked<L>& pv, const VRegs<L>& r, int lane) {
+__device__ __forceinline__ void vt_transpose(VtPacked& pv, const VRegs& r, int lane) {
     u32x4_t E[2];
     onehot_pair(E, lane);
 #pragma unroll
-    for (int i = 0; i < VRegs<L>::N; ++i)
+    for (int i = 0; i < VRegs::N; ++i)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const f32x4_t d = mfma16(r.v[i], E[h], f32x4_t{});
@@ -117,7 +112,6 @@ __device__ __forceinline__ void vt_transpose(VtPacked<L>& pv, const VRegs<L>& r,
         }
 }
 
-template <int L>
 __device__ __forceinline__ void load_gates(float& gi, float& gf, const SeqRsrc& R, int t0, int lane) {
     const uint32_t goff = static_cast<uint32_t>(t0 + lane) * 4;   // range-checked: zero past the end
     gi = bloadf(R.ig, goff, 0);
@@ -137,10 +131,10 @@ __device__ __forceinline__ void load_gates(float& gi, float& gf, const SeqRsrc& 
 // survive), every row keeps R, its last restart at or before it, and the row's maxima, weights
 // and entry-state terms cover only the tokens from R on.  A chunk that holds a restart drops
 // its entry state: C and n are scaled by zero before this chunk's keys are added.
-template <int L, bool kF32N>
-__device__ __forceinline__ void gate_phase(GateBuf<L, kF32N>& Gb, float gi, float gf, float& m_prev,
+template <bool kF32N>
+__device__ __forceinline__ void gate_phase(GateBuf<kF32N>& Gb, float gi, float gf, float& m_prev,
                                            float& s_cur, int lane, int nvalid, float renorm = kRenorm) {
-    static_assert(L == 64, "one token per lane");
+    static_assert(kL == 64, "one token per lane");
     const bool ok = lane < nvalid;
     const float lg = ok ? flogsig(gf) : 0.0f;
     const bool rs = (lg == -INFINITY);

@@ -390,7 +390,7 @@ __device__ __forceinline__ int64_t dtile_c0(int d0, int dt, int vq, int pp, int 
 
 // ---- x: X = dH C^T on the entry states -----------------------------------------------------------
 // One workgroup of 8 waves per (sequence, 64-row d tile, segment), with the gate phase and lazy scale of
-// chunk_mfma_kernel<64> (C = C_acc e^{s}).  Per chunk: X^T = C dH^T with C as a bf16 pair hi + lo, then
+// chunk_mfma_kernel (C = C_acc e^{s}).  Per chunk: X^T = C dH^T with C as a bf16 pair hi + lo, then
 // C += (w e^{-s} K)^T V with the weighted keys as a bf16 pair (products to about 2^-17 rather than the 2^-9
 // of one rounding, because the backward's gradients can cancel against the state).  The
 // weights go on K, whose tile is 64 columns wide, rather than on V: half the operand reads of the update.
@@ -401,7 +401,7 @@ struct XSmem {
     uint16_t Vt[kDV * kTP];        // the chunk's V^T, rows in pair order
     uint16_t dH[kBL * kRP];        // the chunk's dH rows, then the exchange of the partial products
     uint16_t Kw[2][kBL * 68];      // w e^{-s} K rows of this d tile as bf16 hi, lo (136-byte pitch)
-    GateBuf<64, true> G[2];        // by chunk parity
+    GateBuf<true> G[2];        // by chunk parity
 };
 static_assert(sizeof(XSmem) <= 160 * 1024, "LDS budget");
 // the waves' partial sums of n (kWaves x 64 floats) take the place of the dH rows behind the exchange
@@ -497,18 +497,18 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
     };
     if (c_begin < c_end) {
         const int t0 = c_begin * kBL;
-        load_gates<64>(gi, gf, P, t0, lane);
+        load_gates(gi, gf, P, t0, lane);
         load(t0, tid);
         load_rows512(rdhv, rdh, t0, tid);
         load_pieces<8>(rv, P.v, kDV * 2, t0, wave, lane);
         if (gate_wave) gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0);
-        load_gates<64>(gi, gf, P, t0 + kBL, lane);   // gates are loaded a chunk before their phase
+        load_gates(gi, gf, P, t0 + kBL, lane);   // gates are loaded a chunk before their phase
     }
     const int tid_outer = tid;
     for (int c = c_begin; c < c_end; ++c) {
         MLSTM_OPAQUE_LANES(tid_outer);
         const int t0 = c * kBL;
-        const GateBuf<64, true>& Gc = S.G[c & 1];
+        const GateBuf<true>& Gc = S.G[c & 1];
         __syncthreads();   // the previous chunk's readers are done; this chunk's gates are visible
         store_rows512(S.dH, rdhv, tid);
         store_transposed<8>(S.Vt, rv, wave, lane);
@@ -544,7 +544,7 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_x_kernel(BwdParams A) {
         __syncthreads();   // the chunk's operands are visible
         // gates of the next chunk, one chunk ahead
         if (gate_wave && c + 1 < c_end) gate_phase(S.G[(c + 1) & 1], gi, gf, g_m, g_s, lane, A.T - (t0 + kBL));
-        load_gates<64>(gi, gf, P, t0 + 2 * kBL, lane);
+        load_gates(gi, gf, P, t0 + 2 * kBL, lane);
 
         f32x4_t X[2][4];
         dtile_product<true>(X, C, S.dH, vq, lane, [&](int pp) {

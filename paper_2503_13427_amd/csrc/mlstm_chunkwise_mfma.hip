@@ -69,30 +69,28 @@
 namespace mlstm {
 namespace {
 
-template <int L>
 struct Smem {
-    using C = Cfg<L>;
+    using C = Cfg;
     // d-block set s: Q [tau * QP + d], then K the same way; d block p uses set p % 2
     uint16_t QK[2][2 * C::QKE];
     // [0] V^T[v][tau] and [1] (w e^{-s} V)^T[v][tau] of the current chunk (this workgroup's 128 columns)
     uint16_t Vs[2][kDVT * C::TP];
-    uint16_t St[L * C::SP];                        // S~[tau][sig]
+    uint16_t St[kL * C::SP];                        // S~[tau][sig]
     uint16_t nb[2][2][kDQK];                       // normaliser as bf16 hi / lo rows, double-buffered
     float n[2][kDQK];                              // fp32 normaliser, double-buffered across chunks
-    float dq[L];                                   // Q n_{k-1} (unscaled q)
-    float rs[L * (L / 16)];                        // row sums of S~ per (sigma block, tau)
-    __device__ float& rsum_at(int tau, int sb) { return rs[sb * L + tau]; }
-    GateBuf<L> G[2];                               // by chunk parity
+    float dq[kL];                                   // Q n_{k-1} (unscaled q)
+    float rs[kL * (kL / 16)];                        // row sums of S~ per (sigma block, tau)
+    __device__ float& rsum_at(int tau, int sb) { return rs[sb * kL + tau]; }
+    GateBuf<false> G[2];                               // by chunk parity
     // partial read-outs exchanged between the two d partitions of a column group (DH = 2):
     // [column group][v tile][tau tile][lane] as float4
-    float X[C::NVG * C::VT * (L / 16) * 64 * 4];
+    float X[C::NVG * C::VT * (kL / 16) * 64 * 4];
 };
-static_assert(sizeof(Smem<64>) <= 160 * 1024, "LDS budget");
+static_assert(sizeof(Smem) <= 160 * 1024, "LDS budget");
 
 // Per-thread staging registers: one Q/K d block in flight (V: VRegs).
-template <int L>
 struct QKRegs {
-    static constexpr int N = (L * Cfg<L>::DB / 8) / kThreads;   // 16-byte pieces per thread per matrix
+    static constexpr int N = (kL * Cfg::DB / 8) / kThreads;   // 16-byte pieces per thread per matrix
     u32x4_t q[N];
     u32x4_t k[N];
 };
@@ -103,40 +101,37 @@ struct QKRegs {
 // sequence fall outside the buffer range and read as zero in a partial last chunk; the scalar offset
 // carries only the column base.  Row strides (bytes) come from the call: q, k and v may be strided
 // views of one projection output.
-template <int L>
-__device__ __forceinline__ void load_qk(QKRegs<L>& r, const SeqRsrc& R, int t0, int p, int tid, uint32_t rq,
+__device__ __forceinline__ void load_qk(QKRegs& r, const SeqRsrc& R, int t0, int p, int tid, uint32_t rq,
                                         uint32_t rk) {
-    constexpr int DB = Cfg<L>::DB, PR = DB / 8;   // 16-byte pieces per row
+    constexpr int DB = Cfg::DB, PR = DB / 8;   // 16-byte pieces per row
     const uint32_t soff = p * (DB * 2);
 #pragma unroll
-    for (int i = 0; i < QKRegs<L>::N; ++i) {
+    for (int i = 0; i < QKRegs::N; ++i) {
         const int item = tid + i * kThreads;
         const uint32_t row = static_cast<uint32_t>(t0 + item / PR), col = 16 * (item % PR);
         r.q[i] = bload128(R.q, row * rq + col, soff);
         r.k[i] = bload128(R.k, row * rk + col, soff);
     }
 }
-template <int L>
-__device__ __forceinline__ void store_qk(uint16_t* Qd, uint16_t* Kd, const QKRegs<L>& r, int tid) {
-    constexpr int PR = Cfg<L>::DB / 8, QP = Cfg<L>::QP;
+__device__ __forceinline__ void store_qk(uint16_t* Qd, uint16_t* Kd, const QKRegs& r, int tid) {
+    constexpr int PR = Cfg::DB / 8, QP = Cfg::QP;
 #pragma unroll
-    for (int i = 0; i < QKRegs<L>::N; ++i) {
+    for (int i = 0; i < QKRegs::N; ++i) {
         const int item = tid + i * kThreads;
         const int off = (item / PR) * QP + 8 * (item % PR);
-        MLSTM_CHECK(off >= 0 && off + 8 <= Cfg<L>::QKE, kDbgChunkMfma);
+        MLSTM_CHECK(off >= 0 && off + 8 <= Cfg::QKE, kDbgChunkMfma);
         *reinterpret_cast<u32x4_t*>(&Qd[off]) = r.q[i];
         *reinterpret_cast<u32x4_t*>(&Kd[off]) = r.k[i];
     }
 }
 // (w V)^T from the packed V^T: row weights wC of the chunk, rounded to bf16 once
-template <int L>
-__device__ __forceinline__ void vt_store_scaled(uint16_t* VwT, const VtPacked<L>& pv, const float* wC, int wave,
+__device__ __forceinline__ void vt_store_scaled(uint16_t* VwT, const VtPacked& pv, const float* wC, int wave,
                                                 int lane) {
-    constexpr int TP = Cfg<L>::TP;
+    constexpr int TP = Cfg::TP;
     const int l16 = lane & 15, g16 = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < VRegs<L>::N; ++i) {
-        const int a = wave & 3, b = v_piece_b<L>(wave, i);
+    for (int i = 0; i < VRegs::N; ++i) {
+        const int a = wave & 3, b = v_piece_b(wave, i);
         const int tau = 16 * a + 4 * g16;
         const f32x4_t w = *reinterpret_cast<const f32x4_t*>(&wC[tau]);
 #pragma unroll
@@ -150,13 +145,12 @@ __device__ __forceinline__ void vt_store_scaled(uint16_t* VwT, const VtPacked<L>
         }
     }
 }
-template <int L>
-__device__ __forceinline__ void vt_store_plain(uint16_t* VtT, const VtPacked<L>& pv, int wave, int lane) {
-    constexpr int TP = Cfg<L>::TP;
+__device__ __forceinline__ void vt_store_plain(uint16_t* VtT, const VtPacked& pv, int wave, int lane) {
+    constexpr int TP = Cfg::TP;
     const int l16 = lane & 15, g16 = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < VRegs<L>::N; ++i) {
-        const int a = wave & 3, b = v_piece_b<L>(wave, i);
+    for (int i = 0; i < VRegs::N; ++i) {
+        const int a = wave & 3, b = v_piece_b(wave, i);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             MLSTM_CHECK(32 * b + 16 * h + l16 < kDVT && 16 * a + 4 * g16 + 4 <= TP, kDbgChunkMfma);
@@ -195,7 +189,7 @@ struct ChunkKernelArgs {
 // row pitch (floats) of the entry-state staging of a 256 x 128 tile in LDS: 528 bytes puts the
 // rows 8 apart that one read of the accumulator pickup touches in different banks
 constexpr int kStageP = kDVT + 4;
-static_assert(kDQK * kStageP * 4 <= sizeof(Smem<64>), "staging");
+static_assert(kDQK * kStageP * 4 <= sizeof(Smem), "staging");
 
 
 // Staging order (one Q/K block and one V chunk in registers at a time): block 0 of a chunk is stored during
@@ -207,16 +201,15 @@ static_assert(kDQK * kStageP * 4 <= sizeof(Smem<64>), "staging");
 // branch the compiler cannot count the loads in flight and waits for all of them, and a harmless change of
 // the code around has moved such a wait right behind the loads (950 instead of 795 us for 8 x 8192 tokens).
 // What the loads feed is left out in the last chunk (with it, calls of one chunk took 13.4 instead of 13.0 us).
-template <int L>
 __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs A) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    Smem<L>& S = *reinterpret_cast<Smem<L>*>(smem_raw);
-    using CF = Cfg<L>;
-    constexpr int QP = CF::QP, SP = CF::SP, NB = L / 16, DB = CF::DB, DT = CF::DT, NDB = CF::NDB;
+    Smem& S = *reinterpret_cast<Smem*>(smem_raw);
+    using CF = Cfg;
+    constexpr int QP = CF::QP, SP = CF::SP, NB = kL / 16, DB = CF::DB, DT = CF::DT, NDB = CF::NDB;
     constexpr int NT_S = NB * (NB + 1) / 2;          // causal 16x16 tiles of S^T
     constexpr int MAXT = (NT_S + kWaves - 1) / kWaves;
-    constexpr int NTT = L / 16;                       // 16-wide tau tiles
-    constexpr int NKS = L / 32;                       // k steps of 32 along the chunk
+    constexpr int NTT = kL / 16;                       // 16-wide tau tiles
+    constexpr int NKS = kL / 32;                       // k steps of 32 along the chunk
     constexpr int NUT = (DB / 16 + kWaves - 1) / kWaves;   // 16-col n-update tiles per wave per block
 
     const int tid = threadIdx.x;
@@ -245,7 +238,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
     const int g = sg % A.G;
     const int s = sg / A.G;
     const int v0 = tile * kDVT;
-    const int nc_total = (A.T + L - 1) / L;   // the last chunk may be partial
+    const int nc_total = (A.T + kL - 1) / kL;   // the last chunk may be partial
     const int c_begin = g * A.seg_chunks;
     const int c_end = min(nc_total, c_begin + A.seg_chunks);
 
@@ -322,23 +315,23 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
     float g_m = m_prev, g_s = 0.0f;
     float gi = 0.f, gf = 0.f;
 
-    QKRegs<L> rqk;
-    VRegs<L> rv;
-    VtPacked<L> pv;   // the next chunk's V^T, packed, until its stores
+    QKRegs rqk;
+    VRegs rv;
+    VtPacked pv;   // the next chunk's V^T, packed, until its stores
     if (c_begin < c_end) {
-        const int t0 = c_begin * L;
-        load_qk<L>(rqk, P, t0, 0, tid, A.rq, A.rk);
+        const int t0 = c_begin * kL;
+        load_qk(rqk, P, t0, 0, tid, A.rq, A.rk);
         if (gate_wave) {
-            load_gates<L>(gi, gf, P, t0, lane);
+            load_gates(gi, gf, P, t0, lane);
             gate_phase(S.G[c_begin & 1], gi, gf, g_m, g_s, lane, A.T - t0, c_begin == A.eager_chunk ? kRenormAlways : kRenorm);
         }
-        store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
-        load_v_tr<L>(rv, P, t0, v0, wave, lane, A.rv);
-        vt_transpose<L>(pv, rv, lane);
+        store_qk(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
+        load_v_tr(rv, P, t0, v0, wave, lane, A.rv);
+        vt_transpose(pv, rv, lane);
         __syncthreads();   // the first chunk's gates are visible
-        vt_store_scaled<L>(S.Vs[1], pv, S.G[c_begin & 1].wC, wave, lane);
-        vt_store_plain<L>(S.Vs[0], pv, wave, lane);
-        load_qk<L>(rqk, P, t0, 1, tid, A.rq, A.rk);
+        vt_store_scaled(S.Vs[1], pv, S.G[c_begin & 1].wC, wave, lane);
+        vt_store_plain(S.Vs[0], pv, wave, lane);
+        load_qk(rqk, P, t0, 1, tid, A.rq, A.rk);
     }
     if (slot_entry) {
         // a segment entry slot (four rows interleaved): each accumulator tile is one 16-byte load
@@ -357,17 +350,17 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         // transpose-read lane roles inside a 16-lane group (16x16x32 operands)
         const int tr_row = (l16 >> 2) + 8 * g16;   // + 4r + k base
         const int tr_col = 4 * (l16 & 3);           // + m/n base
-        const int t0 = c * L;
+        const int t0 = c * kL;
         const int cur = (c - c_begin) & 1;
         const int par = c & 1;
-        const GateBuf<L>& Gc = S.G[par];
+        const GateBuf<false>& Gc = S.G[par];
         __syncthreads();   // the previous chunk is done; block 0, V and the gates of this chunk are visible
         // block 1 -> set 1 (its readers in the previous chunk, the last d block and S~, are done)
-        store_qk<L>(S.QK[1], S.QK[1] + CF::QKE, rqk, tid);
-        const int tn = min(c + 1, c_end - 1) * L;   // the next chunk
-        load_gates<L>(gi, gf, P, tn, lane);
+        store_qk(S.QK[1], S.QK[1] + CF::QKE, rqk, tid);
+        const int tn = min(c + 1, c_end - 1) * kL;   // the next chunk
+        load_gates(gi, gf, P, tn, lane);
         // this chunk's plain V^T (its readers in the previous chunk are done); the next chunk's V
-        if (c > c_begin) vt_store_plain<L>(S.Vs[0], pv, wave, lane);
+        if (c > c_begin) vt_store_plain(S.Vs[0], pv, wave, lane);
         const float decay_n = Gc.scal[0];
         const float m_next = Gc.scal[1];
         const float s_new = Gc.scal[2];
@@ -393,8 +386,8 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
                 __syncthreads();   // block p visible, block p - 1 fully read
                 // block 0 of the next chunk; its V, transposed in registers
                 if (c + 1 < c_end) {
-                    store_qk<L>(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
-                    vt_transpose<L>(pv, rv, lane);
+                    store_qk(S.QK[0], S.QK[0] + CF::QKE, rqk, tid);
+                    vt_transpose(pv, rv, lane);
                 }
             }
             // (i) S^T += K_p Q_p^T on this wave's causal tiles
@@ -413,7 +406,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
                                          *reinterpret_cast<const u32x4_t*>(qb + 32 * ks), Sacc[i]);
                 }
             }
-            load_qk<L>(rqk, P, tn, p, tid, A.rq, A.rk);   // the next chunk's block p
+            load_qk(rqk, P, tn, p, tid, A.rq, A.rk);   // the next chunk's block p
             // Q n_{k-1} over this d block: A = Q rows, B = n as bf16 hi / lo columns
             if (dq_wave) {
                 const uint16_t* qa = &Qs[(16 * dqt + l16) * QP + 8 * g16];
@@ -449,7 +442,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
                     alo[vt][3] = pack_bf16x2(c1[2] - lo_f32(a[vt][3]), c1[3] - hi_f32(a[vt][3]));
                 }
                 const int dq0 = 32 * (pt * DH + dh) + 8 * g16;   // within the block
-                if (p == 0 && pt == 0) load_v_tr<L>(rv, P, tn, v0, wave, lane, A.rv);
+                if (p == 0 && pt == 0) load_v_tr(rv, P, tn, v0, wave, lane, A.rv);
                 // the Q operand of the next tau tile is requested before this one's MFMAs are issued
                 // (the scheduling fence keeps the compiler from waiting on each read in turn)
                 u32x4_t b = *reinterpret_cast<const u32x4_t*>(&Qs[l16 * QP + dq0]);
@@ -529,7 +522,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         // barrier, so the gate wave issues ahead of its SIMD partner meanwhile
         if (gate_wave && c + 1 < c_end) {
             __builtin_amdgcn_s_setprio(1);
-            gate_phase(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + L), c + 1 == A.eager_chunk ? kRenormAlways : kRenorm);
+            gate_phase(S.G[par ^ 1], gi, gf, g_m, g_s, lane, A.T - (t0 + kL), c + 1 == A.eager_chunk ? kRenormAlways : kRenorm);
             __builtin_amdgcn_s_setprio(0);
         }
 
@@ -577,8 +570,8 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
                 u32x2_t o;
                 o[0] = pack_bf16x2(vals[0], vals[1]);
                 o[1] = pack_bf16x2(vals[2], vals[3]);
-                MLSTM_CHECK(tau < L && 16 * sb + 4 * g16 + 4 <= SP &&
-                                tau * SP + 16 * sb + 4 * g16 + 4 <= L * SP,
+                MLSTM_CHECK(tau < kL && 16 * sb + 4 * g16 + 4 <= SP &&
+                                tau * SP + 16 * sb + 4 * g16 + 4 <= kL * SP,
                             kDbgChunkMfma);
                 *reinterpret_cast<u32x2_t*>(&S.St[tau * SP + 16 * sb + 4 * g16]) = o;
                 rsum = sum_rows4(rsum);
@@ -594,7 +587,7 @@ __global__ void __launch_bounds__(kThreads, 1) chunk_mfma_kernel(ChunkKernelArgs
         __syncthreads();
         // the next chunk's scaled V^T (its readers, (iv) of this chunk, are done; the next chunk's
         // weights are visible)
-        if (c + 1 < c_end) vt_store_scaled<L>(S.Vs[1], pv, S.G[par ^ 1].wC, wave, lane);
+        if (c + 1 < c_end) vt_store_scaled(S.Vs[1], pv, S.G[par ^ 1].wC, wave, lane);
         // (ii) N^T = interC * N^T + V^T S~^T, then h = N^T / max(|den|, floor); each
         // d partition finishes the tau tiles T with T % 2 == dh, after adding the other's partial
 #pragma unroll
@@ -1074,8 +1067,8 @@ void set_strides(const ChunkArgs& a, uint32_t& nh_magic, int64_t* sq, int64_t* s
 }
 
 hipError_t launch_chunks(const ChunkKernelArgs& a, int S, hipStream_t stream) {
-    const size_t lds = sizeof(Smem<64>);
-    auto kern = chunk_mfma_kernel<64>;
+    const size_t lds = sizeof(Smem);
+    auto kern = chunk_mfma_kernel;
     static std::atomic<uint64_t> raised{0};
     hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kern), lds, raised);
     if (e != hipSuccess) return e;
