@@ -26,8 +26,8 @@ struct Cfg {
     // row pitch (elements) of Q and K blocks: 288 bytes keep the 16-byte row reads of 16 consecutive rows
     // free of bank conflicts
     static constexpr int QP = DB + 16;
-    static constexpr int SP = kL + 16;               // row pitch of S~ (160 bytes)
-    static constexpr int QKE = kL * QP;              // elements of one Q or K block buffer
+    static constexpr int SP = kL + 16;              // row pitch of S~ (160 bytes)
+    static constexpr int QKE = kL * QP;             // elements of one Q or K block buffer
     // Wave split of the workgroup's 256 x 128 slice of C: DH d partitions x (8 / DH) column
     // groups of VT 16-column tiles.  Two partitions halve the Q and K^T operand reads of
     // (iii) and (iv) at the price of summing the two partial read-outs of (iii) through LDS.
@@ -43,13 +43,13 @@ struct Cfg {
 // the backward, which branches on |q . n + ...| against the floor, so that n's rounding decides rows close to it.
 template <bool kF32N>
 struct alignas(16) GateBuf {
-    float x2[kL];        // (i~ - b) * log2 e
-    float M2[kL];        // M * log2 e (0 for a row with no input at all)
-    int R[kL];           // last restart (forget gate exactly zero) at or before the row, -1: none
-    float interC[kL];    // exp(m_prev - M + s) / sqrt(DQK): scale of C_acc^T Q^T
-    float interN[kL];    // exp(m_prev - M) / sqrt(DQK):     scale of Q n
-    float floorv[kL];    // exp(-(b + M))
-    float wC[kL];        // C-update weights exp(x - M_L - s_new)
+    float x2[kL];       // (i~ - b) * log2 e
+    float M2[kL];       // M * log2 e (0 for a row with no input at all)
+    int R[kL];          // last restart (forget gate exactly zero) at or before the row, -1: none
+    float interC[kL];   // exp(m_prev - M + s) / sqrt(DQK): scale of C_acc^T Q^T
+    float interN[kL];   // exp(m_prev - M) / sqrt(DQK):     scale of Q n
+    float floorv[kL];   // exp(-(b + M))
+    float wC[kL];       // C-update weights exp(x - M_L - s_new)
     std::conditional_t<kF32N, float[kL], uint16_t[2][kL]> wb;   // n-update weights exp(x - M_L): fp32, or bf16 hi / lo rows
     float scal[4];      // [0] n decay, [1] m_next, [2] s_new, [3] eager C scale (1: none)
 };
