@@ -600,9 +600,12 @@ hipError_t launch_f32_mma_typed(const F32Args& a, int S, int L, hipStream_t stre
 }
 
 hipError_t launch_chunk_f32(mlstm_dtype dt, const ChunkArgs& a, hipStream_t stream) {
-    if (f32_mma_supported(a.DQK, a.DV, a.L)) {
+    const int S = a.B * a.NH;
+    // a launch has at most 2^32 - 1 threads; past that (more than a million sequences) the VALU kernel's wider
+    // dv tiles still fit
+    const bool fits = static_cast<int64_t>(S) * (a.DV / 16) * (64 * kMmaW) < (int64_t(1) << 32);
+    if (fits && f32_mma_supported(a.DQK, a.DV, a.L)) {
         const F32Args m{a.q, a.k, a.v, a.ipre, a.fpre, a.C0, a.n0, a.m0, a.T, a.DQK, a.DV, a.h, a.CT, a.nT, a.mT};
-        const int S = a.B * a.NH;
         return dt == MLSTM_BF16 ? launch_f32_mma_typed<bf16_t>(m, S, a.L, stream) : launch_f32_mma_typed<float>(m, S, a.L, stream);
     }
     const int dvt = chunk_f32_tile(a.DQK, a.DV, a.L);

@@ -158,3 +158,23 @@ def test_fp32_kernel_is_causal_in_non_finite_values(L, bad):
     assert np.array_equal(h[:, :at - at % 16], ref[:, :at - at % 16])
     # the bad value's own tile of 16 tokens is summed in another order
     assert np.abs(h[:, :at] - ref[:, :at]).max() <= 1e-6 * np.abs(ref).max()
+
+
+def test_more_sequences_than_the_mfma_kernel_can_launch():
+    """2^22 + 8 sequences of 64 value columns: four workgroups of 256 threads for each would be over 2^32 threads."""
+    S, T, DQK, DV, L = 2 ** 22 + 8, 3, 16, 64, 16
+    gen = torch.Generator(device="cuda").manual_seed(98)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    x = [rnd(S, 1, T, DQK), rnd(S, 1, T, DQK), rnd(S, 1, T, DV), rnd(S, 1, T), rnd(S, 1, T) + 3]
+
+    def fwd(sl):
+        a = [t[sl].contiguous() for t in x]
+        n = a[0].shape[0]
+        out = [torch.full(s, 9.0, device="cuda") for s in ((n, 1, T, DV), (n, 1, DQK, DV), (n, 1, DQK), (n, 1))]
+        _mb().mlstm_chunkwise_fwd(*a, None, None, None, L, *out)
+        torch.cuda.synchronize()
+        return out
+    whole = fwd(slice(0, S))
+    for sl in (slice(0, 64), slice(S - 64, S)):
+        for a, b in zip(whole, fwd(sl)):
+            assert float((a[sl] - b).abs().max()) <= TOL_F32 * float(b.abs().max())
