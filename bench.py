@@ -25,7 +25,7 @@ Extra objects on the same line:
                 us per sequence-token, achieved GB/s vs 8 TB/s;
   decode_b1     mlstm_step at B=1, NH=8 (single-sequence generation), in place;
   decode_output the step returning h = sigmoid(o~) * LayerNorm(h~) w: mlstm_step_output
-                (fused epilogue at B=256; column split + output pass at B=1) against
+                (fused epilogue at B=256; in the column split's second kernel at B=1) against
                 mlstm_step followed by mlstm_output_norm;
   output_norm   the hidden-state output h = sigmoid(o~) * LayerNorm(h~) w + b
                 (mlstm_output_norm) on the T=2048 prefill's h shape and the

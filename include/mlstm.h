@@ -91,7 +91,8 @@ typedef enum {
  *   - otherwise any dtype and sizes whose fp32 working set (a DQK x DVt state
  *     tile, the chunk's Q, K and V, the L x L gate matrix) fits in 64 KB of
  *     LDS for some power-of-two tile DVt dividing DV, e.g. DQK = DV = 16 with
- *     L = 16: the fp32 VALU kernel.
+ *     L = 16: the fp32 kernels (fp64 MFMA where DQK and DV are multiples of 16
+ *     and L is 16, 32 or 64, VALU otherwise).
  *
  * workspace: optional device scratch.  workspace_bytes == 0 runs the fused
  * single-pass kernel.  Otherwise it must be at least
@@ -243,8 +244,8 @@ mlstm_status mlstm_output_norm_tokens(const void* h_tilde, const void* o_pre, in
  * workgroup owns each sequence (enough sequences to fill the chip, e.g. a
  * decode batch of 256 x 8 heads) the norm runs on the h~ row in the step
  * kernel itself, from the unrounded fp32 h~, and h~ never goes to memory;
- * otherwise the step writes h~ into h and the output pass runs on it in place,
- * on the same stream.  Limits and state aliasing as mlstm_step, plus DV <=
+ * otherwise the step writes h~ into h and a second kernel applies the norm to
+ * it in place, on the same stream.  Limits and state aliasing as mlstm_step, plus DV <=
  * 2048; h may not overlap o_pre, weight or bias (MLSTM_ERR_ALIAS), a bad eps
  * or norm is MLSTM_ERR_BAD_SHAPE and a NULL o_pre is MLSTM_ERR_NULL_PTR.
  */

@@ -32,7 +32,8 @@ hipError_t launch_step(mlstm_dtype dt, const void* q, const void* k, const void*
                        hipStream_t stream);
 size_t step_lds_bytes(int DQK, int DV);
 // the step with the output gate and headwise norm of the cell's output (fused when one workgroup
-// owns each sequence's row, else the step and then the output pass in place)
+// owns each sequence's row; with split columns in the step's second kernel, in place; else by the
+// output pass, in place)
 bool step_output_fused(int B, int NH, int DQK, int DV);
 hipError_t launch_step_output(mlstm_dtype dt, const void* q, const void* k, const void* v, const float* ipre,
                               const float* fpre, const float* C, const float* n, const float* m, const void* o_pre,
@@ -63,7 +64,7 @@ hipError_t launch_parallel_bwd(mlstm_dtype dt, const void* q, const void* k, con
                                const float* fpre, const float* dh, int B, int NH, int T, int DQK, int DV, float* dq,
                                float* dk, float* dv, float* dipre, float* dfpre, void* workspace, hipStream_t stream);
 
-// --- chunkwise prefill, fp32 VALU kernel (small heads) -----------------------
+// --- chunkwise prefill, fp32 kernels (small heads) ---------------------------
 struct ChunkArgs {
     const void* q;
     const void* k;

@@ -1,4 +1,4 @@
-"""mlstm_chunkwise_fwd on small heads (the fp32 VALU kernel) against the fp64 oracle.
+"""mlstm_chunkwise_fwd on small heads (the fp32 kernels) against the fp64 oracle.
 
 Covers the tiny fp32 workload (B=1, NH=1, T=64, d=16, L=16) at the fp32 bar of
 1e-5, chunk-size independence, an initial state, T = 0, document resets (f~ = -inf),

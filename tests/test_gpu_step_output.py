@@ -3,7 +3,7 @@ h = sigmoid(o~) * (Norm(h~) w + b) (Eq. 6 with Eq. 9) against the fp64 oracle: t
 (Eqs. 2-5) followed by ``output_gate_norm``.
 
 Many sequences take the fused launch (the norm in the step kernel's epilogue, from the unrounded h~);
-few sequences take the column-split step and the output pass in place.  Per-row bar: 2e-2 for bf16,
+few sequences take the column-split step, whose second kernel norms the row in place.  Per-row bar: 2e-2 for bf16,
 1e-5 for fp32.  The state the call leaves is bit-identical to mlstm_step's.
 """
 import numpy as np
@@ -36,7 +36,7 @@ CASES = [
     # (B, NH, DQK, DV, dtype, norm, affine, steps)
     (64, 8, 256, 512, "bf16", "layer", True, 3),    # 512 sequences: fused epilogue
     (40, 8, 256, 512, "bf16", "rms", False, 2),     # 320 sequences: fused, RMSNorm, no affine
-    (1, 8, 256, 512, "bf16", "layer", True, 3),     # 8 sequences: column split + output pass
+    (1, 8, 256, 512, "bf16", "layer", True, 3),     # 8 sequences: column split, norm in the second kernel
     (300, 1, 64, 128, "f32", "layer", True, 3),     # fp32, fused
     (2, 2, 16, 32, "f32", "rms", True, 2),          # fp32, few sequences
     (1, 4, 32, 2048, "f32", "layer", False, 2),     # the widest row the output takes
